@@ -5,7 +5,8 @@
 // A workgroup of eight waves takes a block of up to 256 rows, or 128: consecutive query tokens
 // of one sequence's chunk times the query heads of one KV head.  It reads every page of the
 // keys those rows can see once, four pages (64 keys) a step: the pages are dequantized by
-// all threads into LDS tiles of high and low fp16 parts (x = hi + lo to about 2^-22 |x|),
+// all threads into LDS tiles of high and low fp16 parts under a power of two per step (x = hi + lo
+// to about 2^-22 |x|, and 2^-35 of the step's largest element),
 // middle readings from the nibbles first, then every COO entry overwrites its element with
 // its true value (the engine's zero-insert and merge of Sec. 5.2), and each wave contracts
 // the tiles with its own 32 rows on v_mfma_f32_32x32x16_f16:
@@ -97,6 +98,7 @@ struct PfSmem {
     __align__(16) uint8_t coo[2][SP][kStage];         // COO bytes of keys, values, by page
     __align__(16) float4 kc[SP * P];                  // key tokens: base, Delta, Gp / 8
     __align__(16) float vc[SP][3][P];                 // value tokens: the same, by page
+    __align__(8) int ex[4][2];                                     // exponents of a step's keys, values (step mod 4)
 };
 
 // KH = 1: 32 rows per wave; KH = 2: waves w and w + 4 share 32 rows, a half of the keys each.
@@ -231,11 +233,20 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     };
 
     // ---- token constants -------------------------------------------------------------------
+    // A step's keys (values) x enter the tiles as x 2^(15 - e), |x| < 2^e for all of them: no part
+    // reaches fp16's largest value (a stored 65504 reads back as up to 65536), and the low parts
+    // of small values are not lost below its smallest.  e follows the step's largest bound; it
+    // stays while that lies within five bits below, so that the outputs, in units of
+    // 2^(e - 15), are rescaled rarely.  Waves 0 and 1 form it (in every wave, for its own
+    // entries, the eight prompts of 200-4096 tokens took 1474 us instead of 1397).
     float i_m = 0.0f, i_d = 0.0f, o_m = 0.0f, o_d = 0.0f;   // the lane's token's Min, Delta (inner, outer)
+    int ex = 15;                      // (waves 0, 1)
+    auto within = [](float t) { return fabsf(t) < 65536.0f ? fabsf(t) : 0.0f; };   // (no value lies past others)
+    const float th_m = fmaxf(within(th[1]), within(th[2])), th_o = fmaxf(within(th[0]), within(th[3]));
     uint32_t run_c = 0;
     bool fit_c = true;
     const uint8_t* mine_c = a.pool;   // the record of the lane's token
-    auto token_phase = [&](const Step& x) {
+    auto token_phase = [&](const Step& x, int st) {
         const bool vt = slot < x.nv;                  // (other slots read as zeros)
         const Tok T = token_consts(meta, th);
         i_m = h2f(meta.w0 & 0xffffu);
@@ -245,13 +256,30 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
         run_c = run;
         fit_c = fit;
         mine_c = x.tok;
-        const float base = vt ? T.base : 0.0f, dm = vt ? T.dm : 0.0f, gp = vt ? 0.125f * T.gp : 0.0f;
-        if (wave == 0) S.kc[lane] = make_float4(base, dm, gp, 0.0f);
-        if (wave == 1) {
+        if (wave >= 2) return;
+        // (non-negative floats, ordered as integers; the maximum itself only where e moves)
+        auto bits = [](float v) { return __float_as_int(v); };
+        int most = max(max(bits(fmaf(15.0f, i_d, i_m)), bits(th_o + fmaf(15.0f, o_d, o_m))),
+                       bits(th_m + fmaf(7.0f, T.dm, h2f(meta.w1 & 0xffffu))));
+        most = vt ? most : 0;
+        if (__builtin_amdgcn_ballot_w64(most >= (127 + ex) << 23) ||
+            !__builtin_amdgcn_ballot_w64(most >= (127 + ex - 5) << 23)) {
+            const int row = row_max(most);
+            const int top = max(max(__builtin_amdgcn_readlane(row, 15), __builtin_amdgcn_readlane(row, 31)),
+                                max(__builtin_amdgcn_readlane(row, 47), __builtin_amdgcn_readlane(row, 63)));
+            if (top > 0) ex = min(max((top >> 23) - 126, -24), 16);
+        }
+        const float unit = __int_as_float((127 + 15 - ex) << 23);
+        const float base = vt ? unit * T.base : 0.0f, dm = vt ? unit * T.dm : 0.0f;
+        const float gp = vt ? 0.125f * unit * T.gp : 0.0f;
+        if (type == 0) {
+            S.kc[lane] = make_float4(base, dm, gp, 0.0f);
+        } else {
             S.vc[pgl][0][slot] = base;
             S.vc[pgl][1][slot] = dm;
             S.vc[pgl][2][slot] = gp;
         }
+        if (lane == 0) S.ex[st & 3][type] = ex;
     };
 
     // ---- dense readings into the tiles, nibbles and COO bytes into the staging area ----------
@@ -311,7 +339,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
 
     // ---- COO entries: their true values over the middle readings ------------------------------
     // Lane = token; the four waves of a type share its entries.
-    auto entry_phase = [&](PfTiles<D>& L) {
+    auto entry_phase = [&](PfTiles<D>& L, int st) {
+        const float unit = __int_as_float((127 + 15 - __builtin_amdgcn_readfirstlane(S.ex[st & 3][type])) << 23);
+        const float t_lo = unit * th[0], t_hi = unit * th[3];
+        i_m *= unit; i_d *= unit; o_m *= unit; o_d *= unit;
         const Run r = unpack_run(run_c);
         const int per = (r.cnt + 3) >> 2, first = per * (wave >> 1);
         const int n = min(per, r.cnt - first);
@@ -331,7 +362,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
             const bool outer = (en & 0x40u) != 0;
             const uint32_t low = ~(uint32_t)((int)(en << 24) >> 31);   // all ones on the lower side
             const float mag = fmaf((float)(nib ^ (low & 15u)), outer ? o_d : i_d, outer ? o_m : i_m);
-            const float edge = outer ? (low ? th[0] : th[3]) : 0.0f;
+            const float edge = outer ? (low ? t_lo : t_hi) : 0.0f;
             const float x = edge + __uint_as_float(__float_as_uint(mag) ^ (low & 0x80000000u));
             hi = (_Float16)x;
             lo = (_Float16)(x - (float)hi);
@@ -416,6 +447,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     const int vis_hi = start + i0;    // keys up to here are seen by every row
     const int vis_lo = a.window > 0 ? max(0, end - a.window) : 0;
     float m = -INFINITY, l = 0.0f;    // reference of the exponentials (lane's row), sum (lane's keys)
+    int eo = 15;                      // the outputs' units: 2^(eo - 15)
     f16v o[VT];
 #pragma unroll
     for (int n = 0; n < VT; ++n)
@@ -428,6 +460,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     // times theirs, stay below 2^14).
     u4 ph[2], pl[2];
     auto scores = [&](const PfTiles<D>& L, int hb, int st, int nv4) {
+        const int2 e2 = *reinterpret_cast<const int2*>(&S.ex[st & 3][0]);
         f16v sc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
@@ -450,12 +483,17 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
             mx = fmaxf(mx, sc[r]);
         }
         mx = fmaxf(mx, other_half(mx));
-        mx = mx == -INFINITY ? mx : sl2 * mx;
+        // (the step's unit is a power of two: as good as unscaled keys)
+        const int ek = __builtin_amdgcn_readfirstlane(e2.x), ev = __builtin_amdgcn_readfirstlane(e2.y);
+        const float sls = sl2 * __int_as_float((127 - 15 + ek) << 23);
+        mx = mx == -INFINITY ? mx : sls * mx;
         const bool up = mx > m + 8.0f;
-        if (__builtin_amdgcn_ballot_w64(up)) {
-            const float alpha = up ? __builtin_amdgcn_exp2f(m - mx) : 1.0f;
+        if (__builtin_amdgcn_ballot_w64(up || ev != eo)) {
+            float alpha = up ? __builtin_amdgcn_exp2f(m - mx) : 1.0f;
             m = up ? mx : m;
             l *= alpha;
+            alpha *= __int_as_float((127 + eo - ev) << 23);   // (into this step's units)
+            eo = ev;
 #pragma unroll
             for (int n = 0; n < VT; ++n) o[n] *= alpha;
         }
@@ -463,7 +501,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
         float sum[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int r = 0; r < 16; r += 2) {
-            float e0 = fmaf(sl2, sc[r], -ms), e1 = fmaf(sl2, sc[r + 1], -ms);
+            float e0 = fmaf(sls, sc[r], -ms), e1 = fmaf(sls, sc[r + 1], -ms);
             if (!full) {   // (a zero scale times a hidden key's -inf)
                 e0 = sc[r] == -INFINITY ? -INFINITY : e0;
                 e1 = sc[r + 1] == -INFINITY ? -INFINITY : e1;
@@ -496,15 +534,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     int nv4 = sn.nv4;                 // valid slots of the pages in the current tiles
     if (n_steps > 0) {
         ld_step(sn);
-        token_phase(sn);
+        token_phase(sn, 0);
         lds_barrier();
         dense_phase(S.tl[0]);
         ld_step(snn);
         lds_barrier();
-        entry_phase(S.tl[0]);
+        entry_phase(S.tl[0], 0);
         sn = snn;
         snn = open_step(2);
-        token_phase(sn);
+        token_phase(sn, 1);
         lds_barrier();
     }
     for (int st = 0; st < n_steps; ++st) {
@@ -543,10 +581,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
         if (!late) contract_b();
         const int nv4_n = sn.nv4;
         if (next) {
-            entry_phase(Tn);
+            entry_phase(Tn, st + 1);
             sn = snn;
             snn = open_step(st + 3);
-            token_phase(sn);
+            token_phase(sn, st + 2);
         }
         if (late) contract_b();
         nv4 = nv4_n;
@@ -555,6 +593,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
 
     // ---- outputs, or this range's partials ------------------------------------------------------------
     l += other_half(l);
+    const float back = __int_as_float((127 - 15 + eo) << 23);   // (waves that share rows end on the same step)
     if constexpr (KH == 2) {
         // waves 4-7 hand their rows' sums to waves 0-3 (the tiles' LDS; all waves are past the
         // last barrier)
@@ -582,7 +621,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     }
     if (!rok) return;
     if (a.n_splits == 1) {
-        const float inv = l > 0.0f ? 1.0f / l : 0.0f;
+        const float inv = l > 0.0f ? back / l : 0.0f;
         float* dst = a.out + row * D;
 #pragma unroll
         for (int n = 0; n < VT; ++n)
@@ -596,8 +635,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
         for (int n = 0; n < VT; ++n)
 #pragma unroll
             for (int b = 0; b < 4; ++b) {
-                *reinterpret_cast<float2*>(&pp[32 * n + 8 * b + 4 * hf]) = make_float2(o[n][4 * b], o[n][4 * b + 1]);
-                *reinterpret_cast<float2*>(&pp[32 * n + 8 * b + 4 * hf + 2]) = make_float2(o[n][4 * b + 2], o[n][4 * b + 3]);
+                *reinterpret_cast<float2*>(&pp[32 * n + 8 * b + 4 * hf]) = make_float2(back * o[n][4 * b], back * o[n][4 * b + 1]);
+                *reinterpret_cast<float2*>(&pp[32 * n + 8 * b + 4 * hf + 2]) = make_float2(back * o[n][4 * b + 2], back * o[n][4 * b + 3]);
             }
         if (hf == 0) {
             pp[D] = (m - 6.0f) * 0.693147180559945309f;

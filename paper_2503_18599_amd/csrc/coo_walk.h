@@ -22,6 +22,16 @@ __device__ __forceinline__ int row_scan16(int x) {
     return x;
 }
 
+// Running maximum of non-negative integers (or the bits of non-negative floats) along each row
+// of 16 lanes (its last lane: the row's).
+__device__ __forceinline__ int row_max(int v) {
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, true));
+    v = max(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, true));
+    return v;
+}
+
 // Per-token constants of the dequantization (thresholds th = lo_o, lo_i, hi_i, hi_o).
 struct Tok {
     float base, dm, gp;   // middle reading: base + u*dm + h*gp

@@ -57,6 +57,28 @@ def test_prefill_blocks(ref, hq, h, d, new, lens, window, paged, kind):
     _run(ref, hq, h, d, new, lens, window, paged, kind)
 
 
+@pytest.mark.parametrize("hq,h,d,new,lens", [(2, 2, 64, 128, [300, 128]),    # 128 rows
+                                             (2, 2, 128, 60, [950, 900]),    # 60 rows in a 128-row block
+                                             (8, 2, 64, 64, [400, 64]),      # 256 rows
+                                             (8, 2, 128, 64, [400, 64])])
+@pytest.mark.parametrize("paged", [False, True])
+def test_prefill_blocks_largest_value(ref, hq, h, d, new, lens, paged):
+    """Stored values of +-65504 read back as up to 65536, past fp16's largest finite value.  (Most
+    of them are hidden from some rows; the scale keeps the scores of the others comparable.)"""
+    c = _case(ref, hq, h, d, lens, "top", seed=3)
+    pool = c.oracle_pool(ref)
+    for w in (0, 1):                           # (tokens 0 and 29 of the first sequence)
+        x = [ref.dequantize_slot(pool, P, h, d, c.thr, int(c.bt[0, t // P]), i, w, t % P) for t in (0, 29) for i in range(h)]
+        assert np.abs(x).max() > 65519
+    _run(ref, hq, h, d, new, lens, paged=paged, kind="top", scale=1e-5)
+
+
+@pytest.mark.parametrize("hq,h,d,new,lens", [(2, 2, 64, 128, [300, 128]), (2, 2, 128, 60, [950, 900]),
+                                             (8, 2, 128, 64, [400, 64])])
+def test_prefill_blocks_small_values(ref, hq, h, d, new, lens):
+    _run(ref, hq, h, d, new, lens, kind="small")
+
+
 @pytest.mark.parametrize("scale", [-0.05, 0.0])
 def test_prefill_blocks_scale(ref, scale):
     _run(ref, 8, 2, 128, 64, [500, 64], scale=scale)

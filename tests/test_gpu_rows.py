@@ -3,9 +3,10 @@ where it can go wrong: row counts around its 16-row tiles, COO streams longer th
 staging area, values and thresholds of very different scales, ranges longer than the
 wave's table of pages.  The reference is the oracle's fp64 decode attention per query token.
 
-Tolerance: weights and corrections carry 22 bits and everything sums in fp32, so the
-2-norm error stays near 1e-6 of the result's (up to 1e-6 seen); 8e-6 leaves room for another
-order of the sums."""
+Tolerance, of each row's own 2-norm: a score is a sum of fp32 roundings of terms up to some 30
+(2^-24 x 30 = 2e-6, several of them), and its error is the relative error of a probability;
+weights and corrections carry 22 bits or more and everything sums in fp32.  2e-5 is ten
+such terms."""
 import dataclasses
 import math
 
@@ -20,7 +21,7 @@ pytestmark = pytest.mark.gpu
 
 DEV = "cuda"
 P = 16
-REL = 8e-6
+REL = 2e-5
 INF = float("inf")
 
 
@@ -37,7 +38,19 @@ def _case(ref, hq, h, d, lens, kind, seed=0):
         k = np.stack([np16(c.k[:256]), np16(c.v[:256])])
         c.thr = ref.calibrate(k[0][None], k[1][None], 0.04, 0.06)
         return c
+    if kind == "small":                        # values whose low fp16 part would be subnormal
+        c.v = (c.v.float() * 1e-4).half()
+        v = np16(c.v[:256]).reshape(8, -1, h, d)   # (averages of runs: thresholds between fp16 numbers)
+        c.calibrate_oracle(ref)
+        c.thr[:, 1] = ref.calibrate(v, v, 0.04, 0.06)[:, 1]
+        return c
     c.calibrate_oracle(ref)
+    if kind == "top":                          # every 29th token of K and V holds fp16's largest value
+        g = torch.Generator().manual_seed(2)
+        for x in (c.k, c.v):
+            at = torch.randint(0, c.d, x.shape[:2], generator=g).unsqueeze(-1)
+            sign = 1.0 - 2.0 * torch.randint(0, 2, at.shape, generator=g)
+            x[::29] = x[::29].scatter(2, at[::29], (65504.0 * sign[::29]).half())
     return c
 
 
@@ -52,9 +65,9 @@ def _cache(B, c, paged):
 
 def _check(got, want):
     got, want = got.astype(np.float64), want.astype(np.float64)
-    # per KV head scale: every row's own norm
-    err = np.linalg.norm(got - want, axis=-1)
-    assert np.all(np.isfinite(got)) and np.all(err <= REL * np.linalg.norm(want, axis=-1).max(axis=0)), float(err.max())
+    assert np.all(np.isfinite(got))
+    rel = np.linalg.norm(got - want, axis=-1) / np.linalg.norm(want, axis=-1)
+    assert rel.max() <= REL, float(rel.max())
 
 
 @pytest.mark.parametrize("hq,h,d,new,lens,window,paged,kind", [
