@@ -114,6 +114,43 @@ def test_rows_decode_d64(ref, hq, h, lens, window, kind):
     _check(got, want)
 
 
+@pytest.mark.parametrize("hq,h,lens,dist,bound", [
+    (32, 8, [57] * 6, "gauss_outlier_ch", 2.08e-7), (16, 8, [900, 1500, 400], "gauss_outlier_ch", 3.46e-7),
+    (32, 8, [57] * 6, "t3_lognormal", 1.71e-7), (16, 8, [900, 1500, 400], "t3_lognormal", 2.82e-7)])
+def test_rows_decode_d64_error(ref, hq, h, lens, dist, bound):
+    """No further from the 64-bit result than 32-bit products and sums are: a kernel that dequantizes
+    to fp32 and sums each score and output in fp32 on the vector units was off by `bound`."""
+    from paper_2503_18599_amd import binding as B
+    w = dataclasses.replace(synth.WORKLOADS[2], n_seqs=len(lens), n_q_heads=hq, n_kv_heads=h, head_dim=64, cid=720,
+                            k_dist=dist, v_dist=dist)
+    c = Case(w, lens=lens)
+    c.calibrate_oracle(ref)
+    cache, bt = _cache(B, c, False)
+    q = torch.randn(len(lens), hq, 64, generator=torch.Generator().manual_seed(6)).half()
+    got = B.decode_attention(cache, q.to(DEV), bt, c.lens.to(DEV), max(lens), 0.125).cpu().numpy()
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, h, 64, c.thr, np16(q), c.bt.numpy(),
+                                np.array(lens, np.int32), np.float32(0.125))
+    err = np.linalg.norm(got.astype(np.float64) - want) / np.linalg.norm(want)
+    assert err <= bound, float(err)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("scale", [-0.05, 0.0])
+def test_rows_scale(ref, d, scale):
+    from paper_2503_18599_amd import binding as B
+    lens, new = [300, 40], 3
+    c = _case(ref, 4, 2, d, lens, "t3", seed=4)
+    cache, bt = _cache(B, c, False)
+    q = torch.randn(2 * new, 4, d, generator=torch.Generator().manual_seed(7)).half()
+    i32 = dict(dtype=torch.int32, device=DEV)
+    got = B.prefill_attention(cache, q.to(DEV), bt, c.lens.to(DEV) - new, torch.tensor([0, new, 2 * new], **i32),
+                              max(lens), scale, window=33).cpu().numpy()
+    pos = np.concatenate([np.arange(n - new, n) for n in lens])
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, 2, d, c.thr, np16(q),
+                                c.bt.numpy()[np.repeat([0, 1], new)], (pos + 1).astype(np.int32), np.float32(scale), window=33)
+    _check(got, want)
+
+
 def test_rows_long_range(ref):
     """Many one-token chunks of one shared 2300-token prefix: the chip is full without cutting
     ranges, so each wave walks all 144 pages, past its 64-page tables twice."""
