@@ -28,7 +28,9 @@ __device__ inline uint16_t value_key_inverse(uint32_t k) {
 
 // Calls f(bits) for every value of the set [T][d] that starts at src, rows H * d apart.
 // VEC: d is a multiple of 8 with at most 8 * kCalThreads values and src is 16-byte aligned:
-// a lane takes eight values per load, d / 8 lanes per row.
+// a lane takes eight values per load, d / 8 lanes per row.  Other sets: one value per load, all
+// lanes busy whatever d (eight runs of 512 tokens x 40 heads x 128, two bytes off an aligned
+// address: 104 us, 610 with one row at a time and d lanes busy).
 template <bool VEC, class F>
 __device__ inline void each_value(const uint16_t* src, int T, int d, int64_t row_stride, F f) {
     if constexpr (VEC) {
@@ -46,8 +48,20 @@ __device__ inline void each_value(const uint16_t* src, int T, int d, int64_t row
             }
         }
     } else {
-        for (int64_t t = 0; t < T; ++t)
-            for (int j = (int)threadIdx.x; j < d; j += kCalThreads) f((uint32_t)src[t * row_stride + j]);
+        // value i of the set on lane i mod kCalThreads, whatever d: a step of kCalThreads values is
+        // dt rows and dj values
+        const int dt = kCalThreads / d, dj = kCalThreads % d;
+        int j = (int)threadIdx.x % d;
+#pragma unroll 4
+        for (int64_t t = (int)threadIdx.x / d; t < T;) {
+            f((uint32_t)src[t * row_stride + j]);
+            t += dt;
+            j += dj;
+            if (j >= d) {
+                j -= d;
+                ++t;
+            }
+        }
     }
 }
 

@@ -35,3 +35,26 @@ def test_calibration_sizes(ref, R, T, H, d, shift, kind):
         want = ref.calibrate(x[0].numpy(), x[1].numpy(), outer, inner)
         got = B.calibrate_thresholds(dev[0], dev[1], outer, inner).cpu().numpy()
         assert np.array_equal(got.view(np.uint32), want.view(np.uint32)), (kind, outer, inner)
+
+
+@pytest.mark.parametrize("d,shift", [(128, 3), (100, 0), (20, 0)])
+def test_calibration_without_whole_chunks_keeps_every_lane_busy(d, shift):
+    """Sets that the 16-byte loads do not take: two-byte loads by every lane cost about twice the
+    aligned set's time per value; rows walked one at a time, d lanes busy, ten times and more."""
+    from paper_2503_18599_amd import binding as B
+
+    def time(dim, off):
+        R, T, H = 8, 512, 40
+        buf = torch.randn(2, R * T * H * dim + 8, generator=torch.Generator("cuda").manual_seed(1), device="cuda").half()
+        k, v = (buf[w][off:off + R * T * H * dim].view(R, T, H, dim) for w in (0, 1))
+        best = float("inf")
+        for _ in range(20):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            B.calibrate_thresholds(k, v, 0.04, 0.06)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]))
+        return best
+
+    assert time(d, shift) / d <= 6.0 * time(128, 0) / 128
