@@ -392,7 +392,7 @@ size_t oaken_prefill_attention_workspace_bytes(int32_t n_tokens, int32_t n_q_hea
     size_t total = 0;
     for (const int32_t rt : oaken::kRowTiles)
         total = std::max(total, prefill_ws(n_tokens, n_q_heads, head_dim,
-                                           oaken::plan_prefill(n_tokens, n_q_heads, n_kv_heads, max_seq_len,
+                                           oaken::plan_prefill(n_tokens, 1, n_q_heads, n_kv_heads, max_seq_len,
                                                                sliding_window, rt)).total);
     return total;
 }
@@ -420,10 +420,10 @@ int oaken_prefill_attention(const oaken_cache* cache, const void* q, int32_t n_q
                                                 sliding_window);
     const size_t need = oaken_prefill_attention_workspace_bytes(n_tokens, n_q_heads, cache->n_kv_heads,
                                                                 cache->head_dim, max_seq_len, sliding_window);
-    const oaken::PrefillPlan p = oaken::plan_prefill(n_tokens, n_q_heads, cache->n_kv_heads, max_seq_len,
+    const oaken::PrefillPlan p = oaken::plan_prefill(n_tokens, n_seqs, n_q_heads, cache->n_kv_heads, max_seq_len,
                                                      sliding_window, rt);
     const PrefillWs w = prefill_ws(n_tokens, n_q_heads, cache->head_dim, p);
-    if (!workspace || workspace_bytes < need)
+    if (!workspace || workspace_bytes < std::max(need, w.total))
         return fail(OAKEN_ERR_WORKSPACE, "prefill attention workspace %zu < %zu bytes", workspace_bytes, need);
     if (reinterpret_cast<uintptr_t>(workspace) % 16 != 0)
         return fail(OAKEN_ERR_INVALID_ARG, "prefill attention workspace not 16-byte aligned");

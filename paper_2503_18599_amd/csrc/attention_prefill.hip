@@ -675,29 +675,36 @@ __global__ __launch_bounds__(1024) void prefill_blocks_kernel(const int32_t* cu_
 
 }  // namespace
 
-PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_q_heads, int32_t n_kv_heads, int32_t max_seq_len,
+PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int32_t max_seq_len,
                          int32_t window, int32_t row_tiles) {
     PrefillPlan p{};
     const int G = n_q_heads / n_kv_heads;
     p.row_tiles = row_tiles;
     p.tokens_per_block = std::max(1, 16 * row_tiles / G);
-    // keys a block can see: its own tokens and everything before them (or a window of W
-    // before its first token)
-    const int64_t span = window > 0 ? std::min<int64_t>(max_seq_len, (int64_t)window + p.tokens_per_block + kPage)
-                                    : max_seq_len;
-    const int max_pages = (int)((span + kPage - 1) / kPage) + 1;
-    const int64_t units = (int64_t)std::max(1, (n_tokens + p.tokens_per_block - 1) / p.tokens_per_block) * n_kv_heads;
-    // Workgroups that keep 256 CUs busy.  Up to 32 rows they are single waves, which leave a
-    // page to a page's latency unless the chip is full: a call with fewer pages than wave slots
-    // cuts its ranges down to two pages.  The larger blocks' partials (520 bytes a row and
-    // range) stay small beside the work of 32 pages.
-    const bool rows = p.row_tiles <= 2;
-    const int64_t target = rows ? 6144 : 512;
-    const int want = (int)std::max<int64_t>(1, (target + units - 1) / units);
-    const int least = rows ? short_range(units, max_pages, 2, 16)
-                           : (int)std::min<int64_t>(32, std::max<int64_t>(8, units * max_pages / 512));
-    p.pages_per_split = std::max(least, (max_pages + want - 1) / want);
-    p.n_splits = (max_pages + p.pages_per_split - 1) / p.pages_per_split;
+    // pages a block can see: those of its own tokens and everything before them, or of a window
+    // of W before its first token, which may start inside a page
+    int64_t pages = ((int64_t)max_seq_len + kPage - 1) / kPage;
+    if (window > 0) pages = std::min<int64_t>(pages, ((int64_t)window + p.tokens_per_block + kPage - 1) / kPage + 1);
+    // row blocks of all KV heads; every sequence with tokens starts one of its own
+    const int64_t units = std::max<int64_t>((n_tokens + p.tokens_per_block - 1) / p.tokens_per_block,
+                                            std::min(n_seqs, n_tokens)) * n_kv_heads;
+    auto parts = [](int64_t all, int64_t n) { return (all + n - 1) / n; };
+    if (row_tiles <= 2) {
+        // Single waves.  A range's partials (520 bytes a row, written and read) cost about as much
+        // as two pages of work.  Where there are waves enough, ranges of ten pages or more
+        // even them out; where they leave slots of the chip empty, ranges of two pages or more
+        // fill it and cut the chain of pages, the longer the more waves there are.  Measured at 40
+        // heads: 16 chunks of 16 tokens at 256 keys, 640 waves, 54 us in ranges of two pages, 45 in
+        // four, 64 in one range; 64 chunks, 2560 waves, 187, 130, 104 us.
+        const int64_t even = std::min(parts(row_tiles == 1 ? 6144 : 4096, units), pages / 10);
+        const int64_t fill = std::min((row_tiles == 1 ? 3072 : 2048) / units, pages / std::max<int64_t>(2, units / 256));
+        p.pages_per_split = (int32_t)parts(pages, std::max<int64_t>({1, even, fill}));
+    } else {
+        // Workgroups that fill a CU each; the partials stay small beside the work of 32 pages.
+        const int64_t least = std::min<int64_t>(32, std::max<int64_t>(8, units * pages / 512));
+        p.pages_per_split = (int32_t)std::max(least, parts(pages, parts(512, units)));
+    }
+    p.n_splits = (int32_t)parts(pages, p.pages_per_split);
     return p;
 }
 

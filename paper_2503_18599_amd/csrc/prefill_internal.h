@@ -31,7 +31,8 @@ struct PrefillArgs {
 struct PrefillPlan {
     int32_t tokens_per_block, pages_per_split, n_splits, row_tiles;
 };
-PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_q_heads, int32_t n_kv_heads, int32_t max_seq_len,
+// More sequences never plan more ranges: the plan of one sequence bounds the workspace.
+PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int32_t max_seq_len,
                          int32_t window, int32_t row_tiles);
 constexpr int32_t kRowTiles[] = {1, 2, 8, 16};
 // The 16-row tiles a block takes for chunks of about n_tokens / n_seqs tokens over contexts of

@@ -151,6 +151,34 @@ def test_rows_scale(ref, d, scale):
     _check(got, want)
 
 
+def one_range(B, call, n_tokens, hq, h, d, max_len, window=0):
+    """The result of call(workspace), after checking that it wrote no split partials: the workspace
+    holds the row-block list (at most 16 bytes a token, and its count), then nothing."""
+    n = int(B.lib().oaken_prefill_attention_workspace_bytes(n_tokens, hq, h, d, max_len, window))
+    ws = torch.full((n + 4096,), 0x5a, dtype=torch.uint8, device=DEV)
+    got = call(ws)
+    untouched = bool((ws[16 * n_tokens + 1024:] == 0x5a).all())
+    assert untouched, "cut into ranges"
+    return got
+
+
+def test_single_tokens_stay_one_range(ref):
+    """1600 chunks of one token over 4 heads are 6400 waves: the chip is full, no range is cut."""
+    from paper_2503_18599_amd import binding as B
+    n, L = 1600, 640
+    c = _case(ref, 4, 4, 128, [L], "t3", seed=2)
+    cache, bt = _cache(B, c, False)
+    q1 = torch.randn(1, 4, 128, generator=torch.Generator().manual_seed(5)).half()
+    i32 = dict(dtype=torch.int32, device=DEV)
+    got = one_range(B, lambda ws: B.prefill_attention(cache, q1.repeat(n, 1, 1).to(DEV), bt.repeat(n, 1),
+                                                      torch.full((n,), L - 1, **i32), torch.arange(n + 1, **i32), L, 0.09,
+                                                      workspace=ws), n, 4, 4, 128, L).cpu().numpy()
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, 4, 128, c.thr, np16(q1), c.bt.numpy(),
+                                np.array([L], np.int32), np.float32(0.09))
+    _check(got[:1], want)
+    assert np.array_equal(got, np.broadcast_to(got[:1], got.shape))
+
+
 def test_rows_long_range(ref):
     """Many one-token chunks of one shared 2300-token prefix: the chip is full without cutting
     ranges, so each wave walks all 144 pages, past its 64-page tables twice."""
