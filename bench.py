@@ -322,19 +322,23 @@ def prefill_bench(args, w, cache, bt, lens, dev, bt_cpu):
     t = e0.elapsed_time(e1) / steps / 1e3
     # one pass over each chunk's visible keys: positions [lo, last] of every KV head
     prefix = outlier_prefix(cache, bt_cpu, n, max_len)
-    # query tokens per row block, by the library's rule: one wave of 16 or 32 rows, or, where
-    # that costs more, workgroups of 128 or 256 rows
+    # query tokens per row block, by the library's rule: one wave of 16 or 32 rows, or, past 64
+    # rows and where the waves cost more, workgroups of 128 or 256 rows
     G = Hq // H
     per_chunk = -(-n_tok // n)
     rows = G * per_chunk
-    pages = -(-(min(max_len, win + per_chunk) if win else max_len) // 16)
-    big = 1000 + 130 * pages if rows <= 128 else -(-rows // 256) * (1000 + 170 * pages)
-    if rows <= 32:
+    waves = -(-rows // 32)
+    keys = min(max_len, win + per_chunk) if win else max_len
+
+    def pages(block_rows):
+        full = waves * n * H >= 4 * 2048
+        return -(-(keys - (max(0, per_chunk - block_rows // G) // 2 if full else 0)) // 16)
+
+    big = 1000 + 130 * pages(128) if rows <= 128 else -(-rows // 256) * (1000 + 170 * pages(256))
+    if rows <= 64:
         block_rows = 16 if rows <= 16 else 32
-    elif 74 * -(-rows // 32) * pages < big:
-        block_rows = 32
     else:
-        block_rows = 128 if rows <= 128 else 256
+        block_rows = 32 if 74 * waves * pages(32) < big else (128 if rows <= 128 else 256)
     tpb = max(1, block_rows // G)
     one_pass, passes = 0, 0
     for s in range(n):

@@ -37,21 +37,27 @@ PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, in
 constexpr int32_t kRowTiles[] = {1, 2, 8, 16};
 // The 16-row tiles a block takes for chunks of about n_tokens / n_seqs tokens over contexts of
 // up to max_seq_len (blocks then hold that many rows at most: longer chunks get more blocks).
-// Up to 32 rows, one wave.  With more, waves of 32 rows at 0.74 us of a CU per page each
-// against workgroups that dequantize a page once for 128 rows (1.3 us a page) or 256 (1.7 us)
-// but take some 10 us to fill their pipeline, one per CU: measured at head_dim 128, 28- and
-// 64-token chunks at 2048 keys and prompts of 30-100 tokens (60 prompts, 40 heads: 164 us in
-// blocks of 128 rows).
+// Up to 64 rows, one wave per 16 or 32 (16 chunks of 40 and 64 tokens x 40 heads at 2048 keys: 470
+// and 468 us in waves, 499 and 501 in workgroups; 30 single tokens beside two prompts of 512:
+// 312 us, 474).  With more, waves of 32 rows at 0.74 us of a CU per page each against workgroups
+// that dequantize a page once for 128 rows (1.3 us a page) or 256 (1.7 us) but take some 10 us to
+// fill their pipeline, one per CU (head_dim 128; at 64 all of them cost about two thirds).  A
+// chunk's blocks see its keys up to their own tokens; where the waves fill the chip several times
+// over (four rounds of 2048) only their average counts, else the longest (256 prompts of 30-100
+// tokens, 32 / 8 heads: 205 us in waves, 249 in workgroups; 60 prompts: 70 and 65).
 inline int32_t prefill_row_tiles(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads,
                                  int32_t max_seq_len, int32_t window) {
-    const int64_t per_chunk = ((int64_t)n_tokens + n_seqs - 1) / std::max<int32_t>(1, n_seqs);
-    const int64_t rows = per_chunk * (n_q_heads / n_kv_heads);
-    if (rows <= 32) return rows <= 16 ? 1 : 2;
-    const int64_t keys = window > 0 ? std::min<int64_t>(max_seq_len, window + per_chunk) : max_seq_len;
-    const int64_t pages = (keys + kPage - 1) / kPage, waves = (rows + 31) / 32;
-    const int64_t big = rows <= 128 ? 1000 + 130 * pages : (rows + 255) / 256 * (1000 + 170 * pages);
-    if (74 * waves * pages < big) return 2;
-    return rows <= 128 ? 8 : 16;
+    const int64_t chunk = ((int64_t)n_tokens + n_seqs - 1) / std::max<int32_t>(1, n_seqs);
+    const int64_t G = n_q_heads / n_kv_heads, rows = chunk * G, waves = (rows + 31) / 32;
+    if (rows <= 64) return rows <= 16 ? 1 : 2;
+    const int64_t keys = window > 0 ? std::min<int64_t>(max_seq_len, window + chunk) : max_seq_len;
+    const bool full = waves * n_seqs * n_kv_heads >= 4 * 2048;
+    auto pages = [&](int64_t block_rows) {
+        const int64_t hidden = full ? std::max<int64_t>(0, chunk - block_rows / G) / 2 : 0;
+        return (keys - hidden + kPage - 1) / kPage;
+    };
+    const int64_t big = rows <= 128 ? 1000 + 130 * pages(128) : (rows + 255) / 256 * (1000 + 170 * pages(256));
+    return 74 * waves * pages(32) < big ? 2 : rows <= 128 ? 8 : 16;
 }
 hipError_t launch_prefill(const PrefillArgs& a, int d, int2* row_blocks, int32_t* n_row_blocks, hipStream_t st);
 // One wave per block of up to 16 or 32 rows (row_tiles 1, 2; attention_rows.hip).

@@ -58,7 +58,7 @@ def test_prefill_blocks(ref, hq, h, d, new, lens, window, paged, kind):
 
 
 @pytest.mark.parametrize("hq,h,d,new,lens", [(2, 2, 64, 128, [300, 128]),    # 128 rows
-                                             (2, 2, 128, 60, [950, 900]),    # 60 rows in a 128-row block
+                                             (2, 2, 128, 70, [950, 900]),    # 70 rows in a 128-row block
                                              (8, 2, 64, 64, [400, 64]),      # 256 rows
                                              (8, 2, 128, 64, [400, 64])])
 @pytest.mark.parametrize("paged", [False, True])
@@ -73,7 +73,7 @@ def test_prefill_blocks_largest_value(ref, hq, h, d, new, lens, paged):
     _run(ref, hq, h, d, new, lens, paged=paged, kind="top", scale=1e-5)
 
 
-@pytest.mark.parametrize("hq,h,d,new,lens", [(2, 2, 64, 128, [300, 128]), (2, 2, 128, 60, [950, 900]),
+@pytest.mark.parametrize("hq,h,d,new,lens", [(2, 2, 64, 128, [300, 128]), (2, 2, 128, 70, [950, 900]),
                                              (8, 2, 128, 64, [400, 64])])
 def test_prefill_blocks_small_values(ref, hq, h, d, new, lens):
     _run(ref, hq, h, d, new, lens, kind="small")
@@ -93,3 +93,41 @@ def test_prefill_blocks_long_range(ref):
     """Enough equal chunks of one shared prefix that its 140 pages stay one range: every wave
     refills its 64-page block tables twice."""
     _run(ref, 4, 4, 128, 65, [2240], repeat=130)
+
+
+def test_prefill_mixed_chunks_cost_little_more_than_apart(ref):
+    """Single tokens beside two prompts (a mean chunk of 33 rows) in one call, against the same rows
+    in two calls: blocks as wide as the prompts' would leave each token a workgroup of its own."""
+    from paper_2503_18599_amd import binding as B
+    H, d = 40, 128
+    lens, new = [1024] * 30 + [512] * 2, [1] * 30 + [512] * 2
+    pages = [n // P for n in lens]
+    g = torch.Generator("cuda").manual_seed(3)
+    thr = B.calibrate_thresholds(*(torch.randn(1, 64, H, d, generator=g, device=DEV).half() for _ in range(2)))
+    cache = B.Cache(sum(pages), H, d, thr)
+    first = np.cumsum([0] + pages)
+    bt = torch.tensor([[f + min(i, n - 1) for i in range(max(pages))] for f, n in zip(first, pages)], dtype=torch.int32, device=DEV)
+    i32 = dict(dtype=torch.int32, device=DEV)
+    k, v = (torch.randn(sum(lens), H, d, generator=g, device=DEV).half() for _ in range(2))
+    B.quantize_kv(cache, k, v, bt, torch.zeros(len(lens), **i32), torch.tensor(np.concatenate([[0], np.cumsum(lens)]), **i32),
+                  max(lens))
+
+    def time(part):
+        n = [new[i] for i in part]
+        q = torch.randn(sum(n), H, d, generator=g, device=DEV).half()
+        args = (bt[list(part)].contiguous(), torch.tensor([lens[i] - new[i] for i in part], **i32),
+                torch.tensor(np.concatenate([[0], np.cumsum(n)]), **i32), max(lens[i] for i in part), d ** -0.5)
+        best = float("inf")
+        for _ in range(15):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            for _ in range(4):
+                B.prefill_attention(cache, q, *args)
+            e[1].record()
+            torch.cuda.synchronize()
+            best = min(best, e[0].elapsed_time(e[1]) / 4)
+        return best
+
+    both, tokens, prompts = time(range(32)), time(range(30)), time(range(30, 32))
+    # (312 us against 174 + 91; 474 in workgroups of 128 rows)
+    assert both <= 1.5 * (tokens + prompts), (both, tokens, prompts)

@@ -78,6 +78,8 @@ def _check(got, want):
     (16, 2, 128, 4, [4, 64, 100], 0, False, "t3"),           # eight heads: 32 rows, two tiles full
     (4, 2, 64, 16, [16, 31, 500], 0, False, "t3"),           # head_dim 64, two tiles full
     (8, 2, 64, 3, [3, 100], 33, True, "t3"),                 # head_dim 64 over sparse pages
+    (2, 2, 128, 33, [33, 200], 0, False, "t3"),              # two blocks, the second with one row
+    (8, 2, 64, 16, [16, 300], 0, False, "t3"),               # 64 rows: two full blocks
     (2, 2, 128, 9, [40, 100], 0, False, "all_coo"),          # 2 KiB of COO per record: read from HBM
     (2, 2, 128, 9, [40, 100], 0, True, "all_coo"),
     (4, 2, 64, 2, [40, 100], 0, False, "all_coo"),
