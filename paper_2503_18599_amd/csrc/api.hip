@@ -368,7 +368,7 @@ int oaken_decode_attention_noalloc(const oaken_cache* cache, const void* q, int3
 }
 
 namespace {
-// Prefill workspace: [split partials][row blocks: int2 per query token][row-block count]
+// Prefill workspace: [split partials][row blocks: int4 per query token][row-block count]
 struct PrefillWs {
     size_t part, blocks, count, total;
 };
@@ -376,7 +376,7 @@ PrefillWs prefill_ws(int32_t n_tokens, int32_t n_q_heads, int32_t head_dim, cons
     PrefillWs w{};
     w.part = p.n_splits > 1 ? round_up_sz((size_t)n_tokens * n_q_heads * p.n_splits * (head_dim + 2) * sizeof(float), 256)
                             : 0;
-    w.blocks = round_up_sz((size_t)n_tokens * 2 * sizeof(int32_t), 256);
+    w.blocks = round_up_sz((size_t)n_tokens * sizeof(int4), 256);
     w.count = 256;
     w.total = w.part + w.blocks + w.count;
     return w;
@@ -435,7 +435,7 @@ int oaken_prefill_attention(const oaken_cache* cache, const void* q, int32_t n_q
     a.block_table = block_table;
     a.start_pos = start_pos;
     a.cu_tokens = cu_tokens;
-    a.row_blocks = reinterpret_cast<const int2*>(ws + w.part);
+    a.row_blocks = reinterpret_cast<const int4*>(ws + w.part);
     a.n_row_blocks = reinterpret_cast<const int32_t*>(ws + w.part + w.blocks);
     a.out = out;
     a.partial = w.part ? reinterpret_cast<float*>(ws) : nullptr;
@@ -459,7 +459,7 @@ int oaken_prefill_attention(const oaken_cache* cache, const void* q, int32_t n_q
     a.spages = cache->sparse_pages;
     a.row_tiles = p.row_tiles;
     const hipStream_t s = static_cast<hipStream_t>(stream);
-    int rc = hip_status(oaken::launch_prefill(a, cache->head_dim, reinterpret_cast<int2*>(ws + w.part),
+    int rc = hip_status(oaken::launch_prefill(a, cache->head_dim, reinterpret_cast<int4*>(ws + w.part),
                                               reinterpret_cast<int32_t*>(ws + w.part + w.blocks), s),
                         "prefill attention launch");
     if (rc != OAKEN_OK || p.n_splits == 1) return rc;

@@ -122,17 +122,12 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     const int h = (int)(blockIdx.x % (uint32_t)a.H);
     const uint32_t rest = blockIdx.x / (uint32_t)a.H;
     const int blk = (int)(rest % (uint32_t)a.max_row_blocks), split = (int)(rest / (uint32_t)a.max_row_blocks);
-    const int n_blocks = *a.n_row_blocks;
-    if (blk >= n_blocks) return;                      // (uniform)
-    // (a chunk's last rows see the most keys: those blocks go out first and the short ones fill
-    // the tail)
-    const int2 rb = a.row_blocks[n_blocks - 1 - blk];
-    const int s = rb.x, i0 = rb.y, G = a.Hq / a.H;
-    const int tok0 = a.cu_tokens[s], start = a.start_pos[s];
-    const int n_tok = min(a.cu_tokens[s + 1] - tok0 - i0, a.tokens_per_block);
+    const int4 rb = a.row_blocks[blk];                // (both loads at once: the list has room for every blk)
+    if (blk >= *a.n_row_blocks) return;               // (uniform)
+    const int s = rb.x, tok = rb.y, n_tok = rb.z, pos = rb.w, G = a.Hq / a.H;   // sequence, first token, tokens, position
     const int n_rows = n_tok * G;
-    const int end = start + i0 + n_tok;               // keys any row sees
-    const int lo_first = a.window > 0 ? max(0, start + i0 + 1 - a.window) : 0;
+    const int end = pos + n_tok;                      // keys any row sees
+    const int lo_first = a.window > 0 ? max(0, pos + 1 - a.window) : 0;
     const int pg0 = lo_first / P + split * a.pages_per_split;
     const int pg_end = min((end + P - 1) / P, pg0 + a.pages_per_split);
     const int n_pages = max(0, pg_end - pg0), n_steps = (n_pages + SP - 1) / SP;
@@ -424,8 +419,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     const int row0 = wrow + q32;                        // this lane's row of the block
     const bool rok = row0 < n_rows, work = wrow < n_rows;   // (work: uniform per wave)
     const int tk = rok ? row0 / G : 0, hd = rok ? row0 % G : 0;
-    const int rpos = start + i0 + tk, rlo = a.window > 0 ? max(0, rpos + 1 - a.window) : 0;
-    const int64_t row = (int64_t)(tok0 + i0 + tk) * a.Hq + h * G + hd;
+    const int rpos = pos + tk, rlo = a.window > 0 ? max(0, rpos + 1 - a.window) : 0;
+    const int64_t row = (int64_t)(tok + tk) * a.Hq + h * G + hd;
     u4 bq[KST];
     {
         const uint16_t* qp = a.q + row * D + 8 * hf;
@@ -444,7 +439,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
             bq[k] = x ^ flip;
         }
     }
-    const int vis_hi = start + i0;    // keys up to here are seen by every row
+    const int vis_hi = pos;           // keys up to here are seen by every row
     const int vis_lo = a.window > 0 ? max(0, end - a.window) : 0;
     float m = -INFINITY, l = 0.0f;    // reference of the exponentials (lane's row), sum (lane's keys)
     int eo = 15;                      // the outputs' units: 2^(eo - 15)
@@ -645,29 +640,42 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     }
 }
 
-// Row blocks: sequence s's chunk of C_s tokens is cut into ceil(C_s / T) blocks of T
-// tokens; block k lists (sequence, first token).  One workgroup, sequences in rounds of
-// 1024 with a workgroup prefix sum of the block counts.
-__global__ __launch_bounds__(1024) void prefill_blocks_kernel(const int32_t* cu_tokens, int n_seqs, int T,
-                                                             int max_row_blocks, int2* row_blocks, int32_t* n_row_blocks) {
-    __shared__ int scan[1024];
+// Row blocks: sequence s's chunk of C_s tokens is cut into ceil(C_s / T) blocks of T tokens.  They
+// are listed backwards: a chunk's last block sees the most keys, goes out first, and the
+// short ones fill the tail.  An entry holds all that a block's workgroup needs before its
+// block table, so that nothing is looked up by sequence there.  One workgroup, sequences in
+// rounds of 1024 with a prefix sum of the block counts (within waves, then over them).
+__global__ __launch_bounds__(1024) void prefill_blocks_kernel(const int32_t* cu_tokens, const int32_t* start_pos,
+                                                             int n_seqs, int T, int max_row_blocks, int4* row_blocks,
+                                                             int32_t* n_row_blocks) {
+    __shared__ int wave_sum[16];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     int base = 0;
     for (int s0 = 0; s0 < n_seqs; s0 += 1024) {
-        const int s = s0 + (int)threadIdx.x;
-        const int C = s < n_seqs ? max(0, cu_tokens[s + 1] - cu_tokens[s]) : 0;
+        const int s = n_seqs - 1 - s0 - (int)threadIdx.x;
+        const int tok0 = s >= 0 ? cu_tokens[s] : 0, C = s >= 0 ? max(0, cu_tokens[s + 1] - tok0) : 0;
+        const int start = s >= 0 ? start_pos[s] : 0;
         const int nb = (C + T - 1) / T;
-        scan[threadIdx.x] = nb;
-        __syncthreads();
-        for (int d = 1; d < 1024; d <<= 1) {
-            const int v = threadIdx.x >= (unsigned)d ? scan[threadIdx.x - d] : 0;
-            __syncthreads();
-            scan[threadIdx.x] += v;
-            __syncthreads();
+        int incl = nb;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int v = __shfl_up(incl, d, 64);
+            incl += lane >= d ? v : 0;
         }
-        const int first = base + scan[threadIdx.x] - nb;
-        for (int j = 0; j < nb; ++j)
-            if (first + j < max_row_blocks) row_blocks[first + j] = make_int2(s, j * T);
-        base += scan[1023];
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            before += w < wave ? wave_sum[w] : 0;
+            all += wave_sum[w];
+        }
+        const int first = base + before + incl - nb;
+        for (int j = 0; j < nb; ++j) {
+            const int i0 = (nb - 1 - j) * T;
+            if (first + j < max_row_blocks) row_blocks[first + j] = make_int4(s, tok0 + i0, min(T, C - i0), start + i0);
+        }
+        base += all;
         __syncthreads();
     }
     if (threadIdx.x == 0) *n_row_blocks = min(base, max_row_blocks);
@@ -708,8 +716,8 @@ PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, in
     return p;
 }
 
-hipError_t launch_prefill(const PrefillArgs& a, int d, int2* row_blocks, int32_t* n_row_blocks, hipStream_t st) {
-    hipLaunchKernelGGL(prefill_blocks_kernel, dim3(1), dim3(1024), 0, st, a.cu_tokens, a.n_seqs, a.tokens_per_block,
+hipError_t launch_prefill(const PrefillArgs& a, int d, int4* row_blocks, int32_t* n_row_blocks, hipStream_t st) {
+    hipLaunchKernelGGL(prefill_blocks_kernel, dim3(1), dim3(1024), 0, st, a.cu_tokens, a.start_pos, a.n_seqs, a.tokens_per_block,
                        a.max_row_blocks, row_blocks, n_row_blocks);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

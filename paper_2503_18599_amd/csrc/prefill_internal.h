@@ -15,7 +15,7 @@ struct PrefillArgs {
     const int32_t* block_table;   // [n_seqs][max_blocks]
     const int32_t* start_pos;     // [n_seqs]
     const int32_t* cu_tokens;     // [n_seqs + 1]
-    const int2* row_blocks;       // (sequence, first chunk token) per row block
+    const int4* row_blocks;       // per row block: sequence, first token, tokens, the first's position
     const int32_t* n_row_blocks;  // number of row blocks (device)
     float* out;                   // fp32 [n_tokens][Hq][d]
     float* partial;               // [n_tokens][Hq][n_splits][d + 2] when n_splits > 1
@@ -59,7 +59,7 @@ inline int32_t prefill_row_tiles(int32_t n_tokens, int32_t n_seqs, int32_t n_q_h
     const int64_t big = rows <= 128 ? 1000 + 130 * pages(128) : (rows + 255) / 256 * (1000 + 170 * pages(256));
     return 74 * waves * pages(32) < big ? 2 : rows <= 128 ? 8 : 16;
 }
-hipError_t launch_prefill(const PrefillArgs& a, int d, int2* row_blocks, int32_t* n_row_blocks, hipStream_t st);
+hipError_t launch_prefill(const PrefillArgs& a, int d, int4* row_blocks, int32_t* n_row_blocks, hipStream_t st);
 // One wave per block of up to 16 or 32 rows (row_tiles 1, 2; attention_rows.hip).
 hipError_t launch_rows(const PrefillArgs& a, int d, hipStream_t st);
 

@@ -196,3 +196,23 @@ def test_rows_long_range(ref):
                                 np.array([L], np.int32), np.float32(0.09))
     _check(got[:1], want)
     assert np.array_equal(got, np.broadcast_to(got[:1], got.shape))
+
+
+@pytest.mark.parametrize("hq,h,d,most", [(4, 4, 128, 4), (8, 2, 64, 40), (32, 4, 128, 21)])
+def test_row_blocks_of_many_sequences(ref, hq, h, d, most):
+    """More sequences than the row-block list takes in one round, empty chunks among them, chunks of
+    several blocks: rows at every position of one cached prefix."""
+    from paper_2503_18599_amd import binding as B
+    n, L = 1500 if most == 4 else 1100, 64
+    c = _case(ref, hq, h, d, [L], "t3", seed=5)
+    cache, bt = _cache(B, c, False)
+    clen = np.array([(i * 5) % most if i % 3 else 0 for i in range(n)])
+    start = np.array([(i * 7) % (L - most + 1) for i in range(n)], np.int32)
+    cu = np.concatenate([[0], np.cumsum(clen)]).astype(np.int32)
+    q = torch.randn(int(cu[-1]), hq, d, generator=torch.Generator().manual_seed(8)).half()
+    got = B.prefill_attention(cache, q.to(DEV), bt.repeat(n, 1), torch.from_numpy(start).to(DEV), torch.from_numpy(cu).to(DEV),
+                              L, 0.1).cpu().numpy()
+    pos = np.concatenate([np.arange(s, s + m) for s, m in zip(start, clen)])
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, h, d, c.thr, np16(q),
+                                c.bt.numpy()[np.zeros(len(pos), int)], (pos + 1).astype(np.int32), np.float32(0.1))
+    _check(got, want)
