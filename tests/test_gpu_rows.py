@@ -137,6 +137,29 @@ def test_rows_decode_d64_error(ref, hq, h, lens, dist, bound):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("big", [65504.0, -65504.0, 600.0])
+def test_rows_hidden_key_of_another_size(ref, d, big):
+    """Keys that share their page with visible ones but lie before the window, or past the query,
+    and score thousands of times as much: no trace of them in the results."""
+    from paper_2503_18599_amd import binding as B
+    lens, new = [45, 70], 4
+    c = _case(ref, 4, 2, d, lens, "t3", seed=9)
+    first = c.cu[:-1].long()
+    c.k[first + torch.tensor([0, 32])] = big   # the first windows of 30 start at keys 12 and 37
+    c.k[first + torch.tensor(lens) - 1] = big  # (the last query sees this one itself)
+    cache, bt = _cache(B, c, False)
+    q = torch.randn(2 * new, 4, d, generator=torch.Generator().manual_seed(10)).half()
+    i32 = dict(dtype=torch.int32, device=DEV)
+    got = B.prefill_attention(cache, q.to(DEV), bt, c.lens.to(DEV) - new, torch.tensor([0, new, 2 * new], **i32),
+                              max(lens), 0.1, window=30).cpu().numpy()
+    pos = np.concatenate([np.arange(n - new, n) for n in lens])
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, 2, d, c.thr, np16(q),
+                                c.bt.numpy()[np.repeat([0, 1], new)], (pos + 1).astype(np.int32), np.float32(0.1), window=30)
+    seen = np.arange(2 * new) % new != new - 1
+    _check(got[seen], want[seen])
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("scale", [-0.05, 0.0])
 def test_rows_scale(ref, d, scale):
     from paper_2503_18599_amd import binding as B
