@@ -2,7 +2,7 @@
 pages and 64-page block tables, over fixed records and on-demand sparse pages, with COO
 streams longer than their staging area, negative and zero scales and unaligned queries.  The
 reference is the oracle's fp64 decode attention per query token; the tolerance is that of
-tests/test_gpu_rows.py (22-bit operands, fp32 sums)."""
+tests/test_gpu_rows.py."""
 import math
 
 import numpy as np
@@ -10,7 +10,7 @@ import pytest
 import torch
 
 from tests.cases import np16
-from tests.test_gpu_rows import _cache, _case, _check
+from tests.test_gpu_rows import _cache, _case, _check, one_range
 
 pytestmark = pytest.mark.gpu
 
@@ -18,23 +18,22 @@ DEV = "cuda"
 P = 16
 
 
-def _run(ref, hq, h, d, new, lens, window=0, paged=False, kind="t3", scale=None, unaligned=False, repeat=1):
+def _run(ref, hq, h, d, new, lens, window=0, paged=False, kind="t3", scale=None, unaligned=False):
     from paper_2503_18599_amd import binding as B
     c = _case(ref, hq, h, d, lens, kind, seed=3)
     cache, bt = _cache(B, c, paged)
     scale = float(np.float32(1 / math.sqrt(d) if scale is None else scale))
-    clen = [min(new, n) for n in lens] * repeat
-    ends = list(lens) * repeat
-    start = np.array([n - m for n, m in zip(ends, clen)], np.int32)
+    clen = [min(new, n) for n in lens]
+    start = np.array([n - m for n, m in zip(lens, clen)], np.int32)
     cu = np.concatenate([[0], np.cumsum(clen)]).astype(np.int32)
     q = torch.randn(int(cu[-1]), hq, d, generator=torch.Generator().manual_seed(3)).half()
     buf = torch.zeros(q.numel() + 8, dtype=torch.float16, device=DEV)
     qd = buf[1 if unaligned else 0:][:q.numel()].view(q.shape)
     qd.copy_(q)
-    got = B.prefill_attention(cache, qd, bt.repeat(repeat, 1), torch.from_numpy(start).to(DEV), torch.from_numpy(cu).to(DEV),
+    got = B.prefill_attention(cache, qd, bt, torch.from_numpy(start).to(DEV), torch.from_numpy(cu).to(DEV),
                               max(lens), scale, window=window).cpu().numpy()
-    seq = np.repeat(np.arange(len(ends)) % len(lens), clen)
-    pos = np.concatenate([np.arange(s, n) for s, n in zip(start, ends)])
+    seq = np.repeat(np.arange(len(lens)), clen)
+    pos = np.concatenate([np.arange(s, n) for s, n in zip(start, lens)])
     want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, h, d, c.thr, np16(q), c.bt.numpy()[seq],
                                 (pos + 1).astype(np.int32), np.float32(scale), window=window)
     _check(got, want)
@@ -89,10 +88,25 @@ def test_prefill_blocks_unaligned_query(ref, new):
     _run(ref, 4, 2, 128, new, [700, 100], unaligned=True)
 
 
-def test_prefill_blocks_long_range(ref):
+@pytest.mark.parametrize("hq,h,d,new", [(4, 4, 128, 65), (4, 2, 128, 65), (4, 4, 64, 65)])
+def test_prefill_blocks_long_range(ref, hq, h, d, new):
     """Enough equal chunks of one shared prefix that its 140 pages stay one range: every wave
-    refills its 64-page block tables twice."""
-    _run(ref, 4, 4, 128, 65, [2240], repeat=130)
+    refills its 64-page block tables twice.  (Physical pages are shuffled: a table refilled from
+    another place reads other keys.)"""
+    from paper_2503_18599_amd import binding as B
+    n, L = 260, 2240
+    c = _case(ref, hq, h, d, [L], "t3", seed=3)
+    cache, bt = _cache(B, c, False)
+    q1 = torch.randn(new, hq, d, generator=torch.Generator().manual_seed(3)).half()
+    i32 = dict(dtype=torch.int32, device=DEV)
+    got = one_range(B, lambda ws: B.prefill_attention(cache, q1.repeat(n, 1, 1).to(DEV), bt.repeat(n, 1),
+                                                      torch.full((n,), L - new, **i32), torch.arange(n + 1, **i32) * new, L,
+                                                      d ** -0.5, workspace=ws), n * new, hq, h, d, L)
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, h, d, c.thr, np16(q1), np.repeat(c.bt.numpy(), new, 0),
+                                np.arange(L - new + 1, L + 1, dtype=np.int32), np.float32(d ** -0.5))
+    _check(got[:new].cpu().numpy(), want)
+    same = bool((got.view(n, new, hq, d) == got[:new]).all())
+    assert same
 
 
 def test_prefill_mixed_chunks_cost_little_more_than_apart(ref):

@@ -204,21 +204,25 @@ def test_single_tokens_stay_one_range(ref):
     assert np.array_equal(got, np.broadcast_to(got[:1], got.shape))
 
 
-def test_rows_long_range(ref):
-    """Many one-token chunks of one shared 2300-token prefix: the chip is full without cutting
-    ranges, so each wave walks all 144 pages, past its 64-page tables twice."""
+@pytest.mark.parametrize("hq,h,d,new", [(16, 2, 128, 2), (16, 2, 128, 4), (16, 2, 64, 2)])
+def test_rows_long_range(ref, hq, h, d, new):
+    """Many short chunks of one shared 2300-token prefix: the chip is full without cutting ranges, so
+    each wave walks all 144 pages, past its 64-page tables twice.  (Physical pages are shuffled: a
+    table refilled from another place reads other keys.)"""
     from paper_2503_18599_amd import binding as B
-    n, L = 1600, 2300
-    c = _case(ref, 4, 4, 128, [L], "t3", seed=2)
+    n, L = 8192 // new, 2300
+    c = _case(ref, hq, h, d, [L], "t3", seed=2)
     cache, bt = _cache(B, c, False)
-    q1 = torch.randn(1, 4, 128, generator=torch.Generator().manual_seed(5)).half()
+    q1 = torch.randn(new, hq, d, generator=torch.Generator().manual_seed(5)).half()
     i32 = dict(dtype=torch.int32, device=DEV)
-    got = B.prefill_attention(cache, q1.repeat(n, 1, 1).to(DEV), bt.repeat(n, 1), torch.full((n,), L - 1, **i32),
-                              torch.arange(n + 1, **i32), L, 0.09).cpu().numpy()
-    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, 4, 128, c.thr, np16(q1), c.bt.numpy(),
-                                np.array([L], np.int32), np.float32(0.09))
-    _check(got[:1], want)
-    assert np.array_equal(got, np.broadcast_to(got[:1], got.shape))
+    got = one_range(B, lambda ws: B.prefill_attention(cache, q1.repeat(n, 1, 1).to(DEV), bt.repeat(n, 1),
+                                                      torch.full((n,), L - new, **i32), torch.arange(n + 1, **i32) * new, L,
+                                                      0.09, workspace=ws), n * new, hq, h, d, L)
+    want = ref.decode_attention(c.oracle_pool(ref), c.num_blocks, P, h, d, c.thr, np16(q1), np.repeat(c.bt.numpy(), new, 0),
+                                np.arange(L - new + 1, L + 1, dtype=np.int32), np.float32(0.09))
+    _check(got[:new].cpu().numpy(), want)
+    same = bool((got.view(n, new, hq, d) == got[:new]).all())
+    assert same
 
 
 @pytest.mark.parametrize("hq,h,d,most", [(4, 4, 128, 4), (8, 2, 64, 40), (32, 4, 128, 21)])
