@@ -196,7 +196,10 @@ int oaken_quantize_kv(const oaken_cache* cache, const void* k_new, const void* v
  *   OUTER: hi_o + value | lo_o - value (upper | lower side).
  * q: fp16 [n_seqs][n_q_heads][head_dim]; out: fp32 [n_seqs][n_q_heads][head_dim].
  * seq_lens: int32 [n_seqs], each in [1, max_seq_len]; block_table as above.
- * Arithmetic is fp32; results match an fp64 evaluation within 2e-3 + 1e-2 |ref|.
+ * Results match an fp64 evaluation within 2e-3 + 1e-2 |ref| (seen: 1e-5 of a row's norm).
+ * Softmax and sums are fp32; the products run on matrix cores with the real operands in
+ * parts: at head_dim 128 weights as four int8 limbs (22 bits), at 64 weights and
+ * corrections as two fp16 parts (22 to 23 bits; no further from fp64 than fp32 products).
  * workspace: oaken_attention_workspace_bytes(n_seqs, n_q_heads, n_kv_heads,
  * head_dim, max_seq_len) bytes, 16-byte aligned (may be NULL when that is 0); it holds
  * the split partials of long sequences.
@@ -239,12 +242,13 @@ int oaken_decode_attention_window(const oaken_cache* cache, const void* q, int32
  * out: fp32 [n_tokens][n_q_heads][head_dim].  Every p + 1 <= max_seq_len.
  * Rows (query token, query head) are processed in blocks: consecutive tokens of one chunk
  * times the query heads of one KV head, 16 or 32 rows on one wave or, where the chunks
- * average more (n_tokens / n_seqs) over long enough contexts, 128 or 256 rows on a workgroup;
- * a longer chunk takes several blocks.  Contracted on fp16 matrix cores with every real
- * operand split into high and low fp16 parts, accumulated in fp32.  A block reads each page
- * of its keys once.
+ * average more than 64 (n_tokens / n_seqs) over long enough contexts, 128 or 256 rows on a
+ * workgroup; a longer chunk takes several blocks.  Contracted on fp16 matrix cores with every
+ * real operand split into high and low fp16 parts under powers of two that keep them in
+ * range, accumulated in fp32.  A block reads each page of its keys once.
  * workspace: oaken_prefill_attention_workspace_bytes(...) bytes, 16-byte aligned (never 0
- * for valid sizes: it holds the row-block list, and split partials of long prefixes).
+ * for valid sizes: it holds the row-block list, and split partials where prefixes are cut
+ * into ranges; the size does not know n_seqs and is the largest that any needs).
  */
 size_t oaken_prefill_attention_workspace_bytes(int32_t n_tokens, int32_t n_q_heads, int32_t n_kv_heads,
                                                int32_t head_dim, int32_t max_seq_len, int32_t sliding_window);

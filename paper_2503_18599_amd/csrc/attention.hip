@@ -110,7 +110,12 @@ SplitPlan plan_splits(int32_t n_seqs, int32_t n_q_heads, int32_t n_kv_heads, int
     // as their partials stay small beside the 32 MiB that the allocation-free call has for them.
     const SplitPlan even = plan(min(fit, 32));
     if ((int64_t)n_seqs * n_q_heads * even.n_splits * (head_dim + 2) * 4 <= (16 << 20)) return even;
-    return plan(max(min(fit, 8192 / (kPage * G)), 1));
+    // Larger calls: ranges of 8192 / G keys.  No kernel needs that limit; it keeps the partials, and
+    // with them the calls that the allocation-free entry point takes, what they have always been
+    // (256 sequences of 512-8192 keys, 32 query / 8 KV heads: 866 us in its 128 pages, 752 in
+    // 32 with 34 MiB of partials; 64 query heads 797 and 763).
+    constexpr int kLongRange = 8192;
+    return plan(max(min(fit, kLongRange / (kPage * G)), 1));
 }
 
 // Waves per row of the combine: about eight ranges per wave, at most eight waves.

@@ -1,6 +1,7 @@
 // Chunked-prefill attention over the quantized cache (the prefill stage also reads the KV
 // cache, Sec. 2.1; the sliding window of Sec. 6.1 applies per query), for chunks of more than
-// 32 rows (query token, query head) per KV head; attention_rows.hip takes the shorter ones.
+// 64 rows (query token, query head) per KV head; attention_rows.hip takes the shorter ones
+// and prompts of a few pages (prefill_row_tiles).
 //
 // A workgroup of eight waves takes a block of up to 256 rows, or 128: consecutive query tokens
 // of one sequence's chunk times the query heads of one KV head.  It reads every page of the

@@ -1,4 +1,4 @@
-// Pieces shared by the attention kernels that read the packed records: a token's
+// Pieces shared by the kernels that read and write the packed records: a token's
 // dequantization constants, its run of COO entries, the wave-local hand-over through LDS
 // and the sub-dword operand selects of the entry walks.
 #pragma once
@@ -61,10 +61,10 @@ __device__ __forceinline__ Tok token_consts(const Meta& mt, const float* th) {
     return T;
 }
 
-// The kernels that use it run one wave per workgroup.  The LDS operations of a wave execute
-// in issue order, so handing data between its lanes through LDS needs no wait at all: only
-// wavefront-scope fences, which keep the compiler from moving memory operations across
-// the hand-over and emit no instructions.  (A workgroup barrier would wait for every
+// Between lanes of one wave (LDS areas that no other wave touches).  The LDS operations of a
+// wave execute in issue order, so handing data between its lanes through LDS needs no wait
+// at all: only wavefront-scope fences, which keep the compiler from moving memory operations
+// across the hand-over and emit no instructions.  (A workgroup barrier would wait for every
 // global load in flight and stall the prefetch pipeline; draining the LDS counter would
 // stall on every outstanding LDS operation.)
 __device__ __forceinline__ void wave_sync() {

@@ -16,6 +16,7 @@
 // Outputs are assembled in LDS and leave in wide stores: K rows as dwords straight from
 // registers, metadata as dwords, V pages (channel-major) and COO streams in 16-byte
 // chunks when the segment starts the page.
+#include "coo_walk.h"
 #include "oaken_internal.h"
 
 #include <hip/hip_fp16.h>
@@ -98,14 +99,6 @@ __device__ inline uint32_t pick(uint64_t c, uint32_t a, uint32_t b) {
     uint32_t r;
     asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(c));
     return r;
-}
-
-// The lanes of one wave hand LDS data to each other: LDS operations of a wave execute in
-// issue order, so only compiler fences are needed.
-__device__ inline void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Codes of the eight elements a lane holds of one vector (Eq. 1-4), the vector spread over
@@ -532,7 +525,7 @@ __global__ __launch_bounds__(256) void quantize_token_kernel(QuantArgs a) {
     const int incl = group_incl_scan<LPV>(cnt, m);
     const int c8 = group_sum<8>(cnt);   // entries of the lane's 64-value chunk
     const int n_coo = group_sum<LPV>(cnt);
-    if (!ok) return;   // (no lane exchange below)
+    if (!ok) return;   // (a vector's lanes leave together: those that stay hand LDS data only to each other)
 
     if (which == 0) {
         uint32_t kw = 0;
