@@ -287,8 +287,9 @@ def variant_sweep(args):
 
 def prefill_bench(args, w, cache, bt, lens, dev, bt_cpu):
     """Chunked-prefill attention: the last C cached tokens of every sequence attend causally
-    over their prefixes.  A row block (rows of query token x query head of one KV head) reads each page of its keys once, so the bytes of one pass over every chunk's
-    visible prefix are the algorithmic bytes when a chunk fits one row block."""
+    over their prefixes.  A row block (rows of query token x query head of one KV head) reads
+    each page of its keys once, so the bytes of one pass over every chunk's visible prefix are
+    the algorithmic bytes when a chunk fits one row block."""
     import numpy as np
     import torch
 

@@ -28,13 +28,13 @@
 // that matrix and vector work overlap.
 // Long prefixes are split into page ranges whose partials the log-sum-exp combine merges.
 //
-// Bound: vector issue and latency.  A step of four pages takes a CU about 15.6 K cycles for 256
-// rows: 5.1 K of matrix work per SIMD, about 6.5 K of vector issue (dequantization 40 %,
-// softmax 25 %), the LDS active 4.2 K.  Measured, against 128-row blocks that walked 16-key
-// pages through four barriers on v_mfma_f32_16x16x16_f16: 16 chunks of 64 tokens at 32K keys,
-// 32 query / 8 KV heads, 3030 -> 1670 us; eight prompts of 200-4096 tokens 2590 -> 1407 us;
-// 64-token chunks of 40 heads at 2048 keys 1293 -> 474 us; head_dim 64, 1000-2000-token
-// prompts 1045 -> 260 us.
+// Bound: vector issue beside the matrix cores.  A step of four pages takes a CU about 15.2 K
+// cycles for 256 rows: on each SIMD 8.7 K of vector issue (dequantization 40 %, softmax 25 %)
+// and 5.1 K of matrix work, which together leave little (two waves a SIMD overlap them only in
+// part), the LDS active 5.6 K.  Measured, against 128-row blocks that walked 16-key pages
+// through four barriers on v_mfma_f32_16x16x16_f16: 16 chunks of 64 tokens at 32K keys, 32 query
+// / 8 KV heads, 3020 -> 1655 us (to 1740 on other cards); eight prompts of 200-4096 tokens
+// 2605 -> 1405 us; one prompt of 1000 tokens at head_dim 64 172 -> 70 us.
 #include "coo_walk.h"
 #include "oaken_internal.h"
 #include "prefill_internal.h"
