@@ -412,6 +412,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
         }
     };
 
+    // (the first step's bytes are requested before the queries: small calls wait for both at once)
+    Step sn = open_step(0), snn = open_step(1);
+    if (n_steps > 0) ld_step(sn);
+
     // ---- rows -----------------------------------------------------------------------------------
     // scores in base-2 units; a negative scale goes into the query's signs
     const float sl2 = fabsf(a.scale) * 1.44269504088896341f;
@@ -526,10 +530,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void pr
     };
 
     // ---- pipeline ----------------------------------------------------------------------------------
-    Step sn = open_step(0), snn = open_step(1);
     int nv4 = sn.nv4;                 // valid slots of the pages in the current tiles
     if (n_steps > 0) {
-        ld_step(sn);
         token_phase(sn, 0);
         lds_barrier();
         dense_phase(S.tl[0]);
