@@ -711,9 +711,12 @@ PrefillPlan plan_prefill(int32_t n_tokens, int32_t n_seqs, int32_t n_q_heads, in
         const int64_t fill = std::min((row_tiles == 1 ? 3072 : 2048) / units, pages / std::max<int64_t>(2, units / 256));
         p.pages_per_split = (int32_t)parts(pages, std::max<int64_t>({1, even, fill}));
     } else {
-        // Workgroups that fill a CU each; the partials stay small beside the work of 32 pages.
+        // Workgroups that fill a CU each; the partials stay small beside the work of 32 pages, and
+        // of 8 where the chip is not full.  Whole ranges of that (a ninth page alone would cost 496
+        // blocks 126 MB of partials), or a shorter last one where few blocks leave most CUs idle.
         const int64_t least = std::min<int64_t>(32, std::max<int64_t>(8, units * pages / 512));
-        p.pages_per_split = (int32_t)std::max(least, parts(pages, parts(512, units)));
+        const int64_t most = units < 64 ? parts(pages, least) : std::max<int64_t>(1, pages / least);
+        p.pages_per_split = (int32_t)(parts(parts(pages, std::min(parts(512, units), most)), SP) * SP);   // (whole steps)
     }
     p.n_splits = (int32_t)parts(pages, p.pages_per_split);
     return p;
