@@ -33,8 +33,8 @@
 // and 5.1 K of matrix work, which together leave little (two waves a SIMD overlap them only in
 // part), the LDS active 5.6 K.  Measured, against 128-row blocks that walked 16-key pages
 // through four barriers on v_mfma_f32_16x16x16_f16: 16 chunks of 64 tokens at 32K keys, 32 query
-// / 8 KV heads, 3020 -> 1655 us (to 1740 on other cards); eight prompts of 200-4096 tokens
-// 2605 -> 1405 us; one prompt of 1000 tokens at head_dim 64 172 -> 70 us.
+// / 8 KV heads, 3030 -> 1670 us (1870 over a cold card's first ten calls); eight prompts of
+// 200-4096 tokens 2605 -> 1400 us; one prompt of 1000 tokens at head_dim 64 172 -> 70 us.
 #include "coo_walk.h"
 #include "oaken_internal.h"
 #include "prefill_internal.h"
